@@ -118,6 +118,7 @@ enum { PHASE_START = 0, PHASE_CAND = 1 };
 enum { ST_CONVERGED = 0, ST_MAX_ITERS = 1, ST_STALLED = 2, ST_DEGENERATE = 3, ST_PRUNED = 4 };
 constexpr int HLEV_DONE = -1;       // finished
 constexpr int HLEV_WAIT = -2;       // finished the pruning level, waiting for the ranking
+constexpr int HLEV_PRUNED = -3;     // finished: not among the keep_top best of the ranking
 enum { MODE_LM = 0, MODE_DIAG = 1 };
 
 // Pose a hypothesis is evaluated at in the next pass: R row-major (9), t (3),
@@ -132,7 +133,7 @@ struct PassArgs {
     int n_items;
     int level;
     const PoseEval *pose;
-    const int *hlev;             // level whose evaluation is pending; -1 finished
+    const int *hlev;             // level whose evaluation is pending; negative: finished or waiting
     float *partials;             // [item][G][kNV]
     const int *run_flag;         // NULL, or 0 when no hypothesis is at this level (the launch has nothing to do)
     // Packed hypothesis tiles (pass variants 3 to 10), or NULL: the tile whose

@@ -52,8 +52,9 @@ hipError_t launch_lift(const float *dsm, int Hd, int Wd, double x0, double y0, d
                        const void *ref_map, int Hr, int Wr, int C, int dtype, double scale, float *x, float *y,
                        float *z, void *ref_out, hipStream_t s);
 
-// Top-K pruning of frames whose hypotheses all finished their pruning level.
-hipError_t launch_prune(const FrameDev *frames, int n_frames, HypState *hs, PoseEval *pose, int *hlev,
+// Top-K pruning of frames whose hypotheses all finished their pruning level;
+// max_M bounds the hypotheses of the frames that prune.
+hipError_t launch_prune(const FrameDev *frames, int n_frames, int max_M, HypState *hs, PoseEval *pose, int *hlev,
                         hipStream_t s);
 
 // Per frame: the LM states and poses under evaluation of the hypotheses whose

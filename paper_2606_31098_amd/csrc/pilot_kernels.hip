@@ -3,6 +3,8 @@
 #include "pilot_kernels.h"
 #include "pilot_lm.h"
 
+#include <algorithm>
+
 namespace pilot {
 
 hipError_t launch_pass_c16(int, const TileConfig &, const PassArgs &, hipStream_t);
@@ -364,7 +366,10 @@ __global__ __launch_bounds__(256) void finalize_kernel(const FrameDev *frames, c
     // not yet finalised and none of its hypotheses is still running.
     const int done = f.done_flag ? *f.done_flag : 0;
     int pending = 0;
-    for (int m = threadIdx.x; m < f.M; m += blockDim.x) pending |= (hlev[f.hyp_base + m] != -1);
+    for (int m = threadIdx.x; m < f.M; m += blockDim.x) {
+        const int h = hlev[f.hyp_base + m];
+        pending |= (h >= 0 || h == HLEV_WAIT);
+    }
     double T0[12], cost0 = 0.0, al0 = 0.0, al1 = 0.0;
     int it0 = 0, st0 = 0;
     const bool has0 = (int)threadIdx.x < f.M;
@@ -434,52 +439,73 @@ __global__ __launch_bounds__(256) void finalize_kernel(const FrameDev *frames, c
     }
 }
 
-// Top-K pruning, one block per frame: once no hypothesis of the frame is
-// still at or before its pruning level (all are waiting or finished), rank
-// the waiting ones by cost (ties to the lower index) and let the keep_top
-// best continue at the next level; the others end as PRUNED.
+// Top-K pruning: once no hypothesis of a frame is still at or before its
+// pruning level (all are waiting or finished), rank the waiting ones by cost
+// (ties to the lower index) and let the keep_top best continue at the next
+// level; the others end as PRUNED.
+//
+// Ranking compares every waiting hypothesis with every other, M^2 comparisons
+// from LDS: in one block that chain is M^2 / 256 iterations long (449 us for
+// the 1210-pose grid, over half of its solve), so a block takes kPruneChunk
+// hypotheses with kPruneLanes lanes each, every lane counting its share of
+// the frame (that solve went from 826 to 378 us).  The blocks of a frame
+// do not wait for each other.  What one of them writes must not change what
+// the others read: they read costs, which no block writes, and the level
+// words, which go from HLEV_WAIT to the next level or to HLEV_PRUNED, both of
+// which still say that the hypothesis is being ranked in this launch (before
+// it none of the frame's hypotheses holds either).  A block whose own
+// hypotheses are not waiting has nothing to do.
 constexpr int kPruneMaxM = 8192;
+constexpr int kPruneBlock = 256;
+constexpr int kPruneLanes = 16;                       // lanes per ranked hypothesis
+constexpr int kPruneChunk = kPruneBlock / kPruneLanes;
 
-__global__ __launch_bounds__(256) void prune_kernel(const FrameDev *frames, HypState *hs, PoseEval *pose,
-                                                     int *hlev)
+__global__ __launch_bounds__(kPruneBlock) void prune_kernel(const FrameDev *frames, HypState *hs, PoseEval *pose,
+                                                            int *hlev)
 {
-    const FrameDev &f = frames[blockIdx.x];
-    if (f.M <= 0 || f.keep_top <= 0) return;
+    const FrameDev &f = frames[blockIdx.y];
+    const int m0 = blockIdx.x * kPruneChunk;
+    if (f.M <= 0 || f.keep_top <= 0 || m0 >= f.M) return;
     __shared__ double s_cost[kPruneMaxM];
     int waiting = 0, busy = 0;
-    for (int m = threadIdx.x; m < f.M; m += blockDim.x) {
+    for (int m = threadIdx.x; m < f.M; m += kPruneBlock) {
         const int h = hlev[f.hyp_base + m];
-        waiting |= (h == HLEV_WAIT);
+        waiting |= (h == HLEV_WAIT && m >= m0 && m < m0 + kPruneChunk);
         busy |= (h >= 0 && h <= f.prune_level);
+        const bool ranked = h == HLEV_WAIT || h == f.prune_level + 1 || h == HLEV_PRUNED;
         const double c = hs[f.hyp_base + m].cost;
-        s_cost[m] = (h == HLEV_WAIT) ? (isnan(c) ? __longlong_as_double(0x7ff0000000000000LL) : c)
-                                     : __longlong_as_double(0x7ff8000000000000LL);   // NaN: not ranked
+        s_cost[m] = ranked ? (isnan(c) ? __longlong_as_double(0x7ff0000000000000LL) : c)
+                           : __longlong_as_double(0x7ff8000000000000LL);   // NaN: not ranked
     }
     if (!__syncthreads_or(waiting) || __syncthreads_or(busy)) return;
-    for (int m = threadIdx.x; m < f.M; m += blockDim.x) {
-        const double cm = s_cost[m];
-        if (isnan(cm)) continue;
-        int better = 0;
-        for (int j = 0; j < f.M; ++j) {
+    const int m = m0 + (int)threadIdx.x / kPruneLanes, q = threadIdx.x % kPruneLanes;
+    const double cm = m < f.M ? s_cost[m] : __longlong_as_double(0x7ff8000000000000LL);
+    int better = 0;
+    if (!isnan(cm))
+        for (int j = q; j < f.M; j += kPruneLanes) {
             const double cj = s_cost[j];
-            better += (!isnan(cj) && (cj < cm || (cj == cm && j < m))) ? 1 : 0;
+            better += (cj < cm || (cj == cm && j < m)) ? 1 : 0;   // false for the unranked (NaN)
         }
-        HypState &s = hs[f.hyp_base + m];
-        if (better < f.keep_top) {
-            s.level = f.prune_level + 1;
-            s.phase = PHASE_START;
-            for (int i = 0; i < 12; ++i) pose[f.hyp_base + m].v[i] = s.T[i];
-            hlev[f.hyp_base + m] = s.level;
-        } else {
-            s.status = ST_PRUNED;
-            hlev[f.hyp_base + m] = HLEV_DONE;
-        }
+#pragma unroll
+    for (int o = kPruneLanes / 2; o >= 1; o >>= 1) better += __shfl_xor(better, o, 64);
+    if (q != 0 || isnan(cm) || hlev[f.hyp_base + m] != HLEV_WAIT) return;
+    HypState &s = hs[f.hyp_base + m];
+    if (better < f.keep_top) {
+        s.level = f.prune_level + 1;
+        s.phase = PHASE_START;
+        for (int i = 0; i < 12; ++i) pose[f.hyp_base + m].v[i] = s.T[i];
+        hlev[f.hyp_base + m] = s.level;
+    } else {
+        s.status = ST_PRUNED;
+        hlev[f.hyp_base + m] = HLEV_PRUNED;
     }
 }
 
-hipError_t launch_prune(const FrameDev *frames, int n_frames, HypState *hs, PoseEval *pose, int *hlev, hipStream_t s)
+hipError_t launch_prune(const FrameDev *frames, int n_frames, int max_M, HypState *hs, PoseEval *pose, int *hlev,
+                        hipStream_t s)
 {
-    hipLaunchKernelGGL(prune_kernel, dim3(n_frames), dim3(256), 0, s, frames, hs, pose, hlev);
+    const dim3 grid((std::min(max_M, kPruneMaxM) + kPruneChunk - 1) / kPruneChunk, n_frames);
+    hipLaunchKernelGGL(prune_kernel, grid, dim3(kPruneBlock), 0, s, frames, hs, pose, hlev);
     return hipGetLastError();
 }
 

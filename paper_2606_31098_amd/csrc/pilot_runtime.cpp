@@ -941,7 +941,7 @@ int enqueue_schedule(pilot_ctx *ctx, const Plan &plan, const DevPtrs &dp, const 
                 HIPCHK(ctx, hipStreamWaitEvent(s, ctx->join_ev[i], 0));
             }
         }
-        if (prunes) HIPCHK(ctx, launch_prune(dp.frames, nf, ws.hs, ws.pose, ws.hlev, s));
+        if (prunes) HIPCHK(ctx, launch_prune(dp.frames, nf, plan.max_M, ws.hs, ws.pose, ws.hlev, s));
         if (pack && l + 1 < plan.max_levels) HIPCHK(ctx, pack_level(l + 1));
     }
     HIPCHK(ctx, launch_finalize(dp.frames, (int)plan.frames.size(), ws.hs, ws.hlev, s));
@@ -1822,11 +1822,12 @@ int pilot_step(pilot_ctx *ctx)
             if (g.level == l && (rc = enqueue_pass(ctx, plan, dp, ws_of(ctx), g, MODE_LM, ctx->stream,
                                                    (ctx->flags & PILOT_FLAG_PROFILE) != 0, nullptr, nullptr, true)))
                 return rc;
-    bool prunes = false;
-    for (const ServingSlot &sl : ctx->slots) prunes = prunes || (sl.active && sl.frame.keep_top > 0);
-    if (prunes)
-        HIPCHK(ctx, launch_prune(dp.frames, (int)ctx->slots.size(), (HypState *)ctx->hs.p, (PoseEval *)ctx->pose.p,
-                                 (int *)ctx->hlev.p, ctx->stream));
+    int prune_M = 0;
+    for (const ServingSlot &sl : ctx->slots)
+        if (sl.active && sl.frame.keep_top > 0) prune_M = std::max(prune_M, sl.M);
+    if (prune_M)
+        HIPCHK(ctx, launch_prune(dp.frames, (int)ctx->slots.size(), prune_M, (HypState *)ctx->hs.p,
+                                 (PoseEval *)ctx->pose.p, (int *)ctx->hlev.p, ctx->stream));
     HIPCHK(ctx, launch_finalize(dp.frames, (int)ctx->slots.size(), (const HypState *)ctx->hs.p,
                                 (const int *)ctx->hlev.p, ctx->stream));
     ctx->steps_enqueued++;
