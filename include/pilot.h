@@ -212,7 +212,8 @@ typedef struct {
     uint64_t pairs[PILOT_MAX_LEVELS];      /* anchor x hypothesis evaluations, per level  */
     uint64_t pair_bytes[PILOT_MAX_LEVELS]; /* algorithmic gathered bytes (4 C s_f/pair)   */
     uint64_t launches[PILOT_MAX_LEVELS];   /* pass launches per level                     */
-    double pass_ms[PILOT_MAX_LEVELS];      /* summed pass durations (PILOT_FLAG_PROFILE)  */
+    double pass_ms[PILOT_MAX_LEVELS];      /* summed durations of the pass launches        */
+                                           /* (PILOT_FLAG_PROFILE), with the LM steps in them */
     uint64_t timed_launches[PILOT_MAX_LEVELS];
     uint64_t graph_replays, graph_captures;
 } pilot_stats;

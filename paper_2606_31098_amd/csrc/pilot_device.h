@@ -147,6 +147,7 @@ struct PassArgs {
     const int *pcount;
     int *pcount_clear;
     int n_frames;
+    int item_blocks;             // blocks that walk the items
 };
 
 struct EpilogueArgs {

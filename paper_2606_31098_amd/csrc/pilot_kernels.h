@@ -19,13 +19,14 @@ struct TileConfig {
 // True if a pass kernel exists for (C, dtype, G).
 bool pass_supported(int C, int dtype, int G);
 
-// One pass over `n_items` work items at `level`, every item a tile of
-// G hypotheses x (kBlock / G * PPG) anchors of frames with C channels:
-// writes the per-item partial sums.
-hipError_t launch_pass(int C, int dtype, const TileConfig &tc, const PassArgs &a, hipStream_t s);
-
-// Per hypothesis tile: FP64 reduction of the partials in item order and the
-// LM step (or, in MODE_DIAG, the diagnostic outputs).
+// One LM pass over `n_items` work items at `level`, every item a tile of
+// G hypotheses x (kBlock / G * PPG) anchors of frames with C channels: the
+// per-item partial sums, then per hypothesis tile their FP64 reduction in item
+// order and the LM step (or, in MODE_DIAG, the diagnostic outputs).  The steps
+// run in the last blocks of the pass launch (pilot_step.inc), or, for the
+// variants without them, in an epilogue launch.
+hipError_t launch_pass(int C, int dtype, const TileConfig &tc, const PassArgs &a, const EpilogueArgs &e,
+                       hipStream_t s);
 hipError_t launch_epilogue(const EpilogueArgs &e, hipStream_t s);
 
 // Initialise hypothesis state of frames[0..n_frames) from their poses_in

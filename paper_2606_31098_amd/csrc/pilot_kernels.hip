@@ -7,11 +7,11 @@
 
 namespace pilot {
 
-hipError_t launch_pass_c16(int, const TileConfig &, const PassArgs &, hipStream_t);
-hipError_t launch_pass_c32(int, const TileConfig &, const PassArgs &, hipStream_t);
-hipError_t launch_pass_c64(int, const TileConfig &, const PassArgs &, hipStream_t);
-hipError_t launch_pass_c128(int, const TileConfig &, const PassArgs &, hipStream_t);
-hipError_t launch_pass_c256(int, const TileConfig &, const PassArgs &, hipStream_t);
+hipError_t launch_pass_c16(int, const TileConfig &, const PassArgs &, const EpilogueArgs &, hipStream_t);
+hipError_t launch_pass_c32(int, const TileConfig &, const PassArgs &, const EpilogueArgs &, hipStream_t);
+hipError_t launch_pass_c64(int, const TileConfig &, const PassArgs &, const EpilogueArgs &, hipStream_t);
+hipError_t launch_pass_c128(int, const TileConfig &, const PassArgs &, const EpilogueArgs &, hipStream_t);
+hipError_t launch_pass_c256(int, const TileConfig &, const PassArgs &, const EpilogueArgs &, hipStream_t);
 
 bool pass_supported(int C, int dtype, int G)
 {
@@ -20,14 +20,15 @@ bool pass_supported(int C, int dtype, int G)
     return C == 16 || C == 32 || C == 64 || C == 128 || C == 256;
 }
 
-hipError_t launch_pass(int C, int dtype, const TileConfig &tc, const PassArgs &a, hipStream_t s)
+hipError_t launch_pass(int C, int dtype, const TileConfig &tc, const PassArgs &a, const EpilogueArgs &e,
+                       hipStream_t s)
 {
     switch (C) {
-    case 16: return launch_pass_c16(dtype, tc, a, s);
-    case 32: return launch_pass_c32(dtype, tc, a, s);
-    case 64: return launch_pass_c64(dtype, tc, a, s);
-    case 128: return launch_pass_c128(dtype, tc, a, s);
-    case 256: return launch_pass_c256(dtype, tc, a, s);
+    case 16: return launch_pass_c16(dtype, tc, a, e, s);
+    case 32: return launch_pass_c32(dtype, tc, a, e, s);
+    case 64: return launch_pass_c64(dtype, tc, a, e, s);
+    case 128: return launch_pass_c128(dtype, tc, a, e, s);
+    case 256: return launch_pass_c256(dtype, tc, a, e, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -237,8 +238,9 @@ __global__ __launch_bounds__(kEpiBlock) void epilogue_kernel(EpilogueArgs e)
         auto home = [&](int hh) -> int { return packed ? s_hs[hh].home : hb + hh; };
         for (int w = threadIdx.x; w < nhs; w += kEpiBlock)
             if ((act >> (w / kHsW)) & 1u) reinterpret_cast<double *>(e.hs + home(w / kHsW))[w % kHsW] = hs_lds[w];
-        if ((int)threadIdx.x < npe && ((act >> (threadIdx.x / kPeW)) & 1u))
-            reinterpret_cast<double *>(e.pose + home(threadIdx.x / kPeW))[threadIdx.x % kPeW] = pe_lds[threadIdx.x];
+        // (the pose alone: its padding holds the step blocks' arrival counter)
+        if ((int)threadIdx.x < npe && ((act >> (threadIdx.x / kPeW)) & 1u) && threadIdx.x % kPeW < 12)
+            e.pose[home(threadIdx.x / kPeW)].v[threadIdx.x % kPeW] = pe_lds[threadIdx.x];
         if (lists) {
             // the survivors' states and next poses, to their entries of the next list
             const unsigned keep = s_keep;

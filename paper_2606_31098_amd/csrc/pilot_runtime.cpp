@@ -823,20 +823,6 @@ int enqueue_pass(pilot_ctx *ctx, const Plan &plan, const DevPtrs &dp, const Ws &
         a.pcount_clear = ws.pcount + (size_t)b2 * ws.frames;
         a.n_frames = ws.frames;
     }
-    TimedLaunch tl{};
-    if (timed) {
-        tl.a = pool_event(ctx);
-        tl.b = pool_event(ctx);
-        tl.level = g.level;
-        tl.cls = g.stat_class;
-        if (!tl.a || !tl.b) return fail(ctx, PILOT_EDEVICE, "hipEventCreate failed");
-        HIPCHK(ctx, hipEventRecord(tl.a, s));
-    }
-    HIPCHK(ctx, launch_pass(g.C, g.dtype, g.tc, a, s));
-    if (timed) {
-        HIPCHK(ctx, hipEventRecord(tl.b, s));
-        ctx->timed.push_back(tl);
-    }
     EpilogueArgs e{};
     e.frames = dp.frames;
     e.tiles = dp.tiles + g.tile_off;
@@ -859,7 +845,20 @@ int enqueue_pass(pilot_ctx *ctx, const Plan &plan, const DevPtrs &dp, const Ws &
         e.ppose_next = ws.ppose + (size_t)b1 * ws.hyps;
         e.pcount_next = ws.pcount + (size_t)b1 * ws.frames;
     }
-    HIPCHK(ctx, launch_epilogue(e, s));
+    TimedLaunch tl{};
+    if (timed) {
+        tl.a = pool_event(ctx);
+        tl.b = pool_event(ctx);
+        tl.level = g.level;
+        tl.cls = g.stat_class;
+        if (!tl.a || !tl.b) return fail(ctx, PILOT_EDEVICE, "hipEventCreate failed");
+        HIPCHK(ctx, hipEventRecord(tl.a, s));
+    }
+    HIPCHK(ctx, launch_pass(g.C, g.dtype, g.tc, a, e, s));
+    if (timed) {
+        HIPCHK(ctx, hipEventRecord(tl.b, s));
+        ctx->timed.push_back(tl);
+    }
     ctx->launches[g.stat_class]++;
     return PILOT_OK;
 }
