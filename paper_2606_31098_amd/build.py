@@ -20,6 +20,9 @@ ARCH = "gfx950"
 HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
              # no packed-FP32 instructions (see the design notes)
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+             # the SLP pass packs a pair's visibility tests into 16-bit vector
+             # arithmetic (a dozen instructions for six compares)
+             "-fno-slp-vectorize",
              "-Wall", "-Wno-unused-function", "-Wno-unused-variable"]
 
 
