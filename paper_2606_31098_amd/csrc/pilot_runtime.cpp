@@ -1364,10 +1364,11 @@ int pilot_autotune(pilot_ctx *ctx, const pilot_frame *frame)
     if ((rc = collect_timings(ctx))) return rc;           // earlier profiled launches go to the counters
 
     std::vector<TileConfig> cand;
-    // variants 5, 6, 8, 9 and 10 differ from 3, 4, 7, 3 and 4 for bf16 maps only
+    // variants 5, 6, 8 and 10 differ from 3, 4, 7 and 4 for bf16 maps only; 9
+    // and 10 are one kernel there
     bool bf16 = false;
     for (int l = 0; l < frame->n_levels; ++l) bf16 = bf16 || frame->level[l].dtype == PILOT_BF16;
-    for (int variant : {1, 2, 3, 4, 5, 6, 7, 8, 9, 10}) {
+    for (int variant : {1, 2, 3, 4, 5, 6, 7, 8, 10}) {
         if ((variant == 5 || variant == 6 || variant >= 8) && !bf16) continue;
         for (int G : {1, 2, 4, 8, 16}) {
             if (G < 4 && variant < 9) continue;          // narrow lane groups: variants 9 and 10 only
