@@ -11,7 +11,8 @@ struct TileConfig {
     int grid = 0;       // blocks per CU of a persistent grid (0: one block per item); launch: blocks
     int variant = 1;    // pass kernel: 1 batch-then-compute loop, 2 software-pipelined loop,
                         // 3-8 per-cell Gram tables (see pilot_pass3.inc), 9-10 the same with
-                        // FP32 arithmetic on the per-pair path for bf16 maps (pilot_pass4.inc)
+                        // FP32 arithmetic on the per-pair path for bf16 maps (pilot_pass4.inc,
+                        // one kernel under both numbers)
     int pack = 0;       // variants 3-10: hypothesis tiles 0 contiguous, 1 packed when that saves
                         // rounds of blocks (use_packed), 2 packed whenever hypotheses remain
 };

@@ -48,3 +48,34 @@ def test_tile_sums_at_batch_edges_match_oracle(tmp_path, G, items, grid):
         err = rel_frobenius(np.concatenate([H[m], g[m][:, None]], 1), np.concatenate([Ho, go[:, None]], 1))
         assert err <= NEQ_TOL, (m, err)
         assert abs(cost[m] - co) <= 1e-9 * abs(co) and n[m] == no, (m, cost[m], co, n[m], no)
+
+
+@pytest.mark.parametrize("C", [32, 64, 128])
+@pytest.mark.parametrize("G", [4, 8, 16])
+@pytest.mark.parametrize("variant", [1, 4])
+def test_groups_that_share_projections_with_most_anchors_unseen_match_oracle(tmp_path, variant, G, C):
+    """A lane group reads its hypotheses' cells from each other's lanes: poses
+    turned so far that some hypotheses see few anchors or none, beside some
+    that see all, in tiles whose last one is ragged."""
+    from paper_2606_31098_amd.pilot import Context, DeviceFrame
+    N, M = 517, G + 3
+    f = S.make_frame(2, 0, N=N, M=M, level_shapes=((60, 80, C),), iters=(2,), dsm_side=256, seed=31)
+    L = f.levels[0]
+    cache = tmp_path / "tune.txt"
+    cache.write_text(f"C{C}_d0_N{floor_log2(N)}_M{floor_log2(M)}_P{floor_log2(L.H * L.W)}_v3 {G} 2 0 {variant} 0\n")
+    ctx = Context(0, tune_cache=str(cache))
+    assert f"G={G} PPG=2" in ctx.tile_choice(C, 0, N, M, L.H * L.W)
+    turns = [0.0, 0.3, 0.6, np.pi]                   # all seen, some, few, behind the camera
+    poses = np.stack([oracle.compose(oracle.se3_exp(np.array([0.1 * m, 0, 0, 0, turns[m % 4], 0])), f.gt_pose)
+                      for m in range(M)])
+    mask_edges(f, poses)
+    say(f"unseen: variant={variant} G={G} C={C}")
+    H21, g, cost, n = ctx.linearize(DeviceFrame(f), 0, torch.as_tensor(poses, device="cuda"))
+    torch.cuda.synchronize()
+    H, g, cost, n = unpack_h21(H21.cpu().numpy()), g.cpu().numpy(), cost.cpu().numpy(), n.cpu().numpy()
+    of = oracle.OracleFrame(f)
+    for m in range(M):
+        Ho, go, co, no = oracle.linearize(of, 0, poses[m])
+        assert n[m] == no and abs(cost[m] - co) <= 1e-9 * abs(co), (m, n[m], no, cost[m], co)
+        err = rel_frobenius(np.concatenate([H[m], g[m][:, None]], 1), np.concatenate([Ho, go[:, None]], 1))
+        assert err <= NEQ_TOL, (m, err)              # nothing seen: the priors' terms alone
