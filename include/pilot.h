@@ -81,7 +81,9 @@ enum {
     PILOT_FLAG_AUTOTUNE = 2,  /* time tile candidates on first use of a shape class     */
     PILOT_FLAG_PROFILE = 4,   /* time every pass launch with hipEvents (implies NO_GRAPH) */
     PILOT_FLAG_KEEP_ORDER = 8,/* walk anchors in the caller's order (no spatial sort)     */
-    PILOT_FLAG_SORT_ANCHORS = 16 /* sort every level's anchors (2..16384 of them)          */
+    PILOT_FLAG_SORT_ANCHORS = 16,/* sort every level's anchors (2..16384 of them)          */
+    PILOT_FLAG_NO_STEP_WAIT = 32 /* LM steps do not wait for other blocks' sums but form    */
+                                 /* them again (the same results, slower)                   */
 };
 
 typedef struct pilot_ctx pilot_ctx;

@@ -122,7 +122,8 @@ constexpr int HLEV_PRUNED = -3;     // finished: not among the keep_top best of 
 enum { MODE_LM = 0, MODE_DIAG = 1 };
 
 // Pose a hypothesis is evaluated at in the next pass: R row-major (9), t (3),
-// 4 pad -> 128 bytes.
+// 4 pad -> 128 bytes.  The padding of the hypotheses' own poses holds arrival
+// counters (pilot_step.inc).
 struct PoseEval {
     double v[16];
 };
@@ -148,6 +149,7 @@ struct PassArgs {
     int *pcount_clear;
     int n_frames;
     int item_blocks;             // blocks that walk the items
+    int count_slot;              // which of a tile's arrival counters this launch uses (pilot_step.inc)
 };
 
 struct EpilogueArgs {
@@ -163,6 +165,8 @@ struct EpilogueArgs {
     HypState *hs;
     unsigned long long *pairs;   // evaluated anchor x hypothesis pairs of this launch's class
     int *next_flag;              // NULL, or set to 1 when a hypothesis stays at this level
+    int step_spins;              // turns (at least 0.3 us each) that a step block waits for its
+                                 // tile's items before it walks them itself
     int mask_first;              // test the tile mask before fetching the partial sums (launches
                                  // where most tiles are at other levels), else after
     // packed hypothesis tiles (as in PassArgs), or NULL: slot hh of the tile
@@ -178,6 +182,13 @@ struct EpilogueArgs {
     PoseEval *ppose_next;
     int *pcount_next;
 };
+
+// The arrival counters of pilot_step.inc: two successive launches with step
+// blocks over a frame use different ones.  turn: the pass of a solve, or the
+// step of a serving loop.
+constexpr int kCountSlots = 2 * kMaxLevels;
+static_assert(kCountSlots * sizeof(unsigned) <= sizeof(PoseEval) - 12 * sizeof(double), "the pose's padding");
+inline int count_slot_of(int level, unsigned long long turn) { return 2 * level + (int)(turn & 1); }
 
 // Packed or contiguous hypothesis tiles for one frame in one pass: packed when
 // the tiles a contiguous walk may find active (at most one per hypothesis

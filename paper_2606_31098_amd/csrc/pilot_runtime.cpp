@@ -164,6 +164,7 @@ struct pilot_ctx {
     size_t serv_bytes = 0;
     bool serv_dirty = true;
     Plan serv_plan;                             // work lists over the active slots
+    uint64_t step_turn = 0;      // counts every step begun (count_slot_of)
     uint64_t steps_enqueued = 0;
     struct FlagBuf {
         int *host = nullptr;
@@ -795,12 +796,19 @@ int ensure_state(pilot_ctx *ctx, Plan &plan)
     return PILOT_OK;
 }
 
+// Turns (about 0.4 us each) that a step block waits for its tile's items before
+// it walks them itself.  It starts when the last items of its XCD have started,
+// so it waits for about one item (5 to 100 us, tens of items where other
+// launches share the device); past 1.6 ms its items are most likely not even
+// placed.
+constexpr int kStepSpins = 1 << 12;
+
 // Enqueue one pass (pass kernel + epilogue) of a launch group.
 // packed: the Gram-table variants (3 to 10) walk packed hypothesis tiles,
 // built by the pack kernel right before the pass.
 int enqueue_pass(pilot_ctx *ctx, const Plan &plan, const DevPtrs &dp, const Ws &ws, const LaunchGroup &g, int mode,
                  hipStream_t s, bool timed, const int *run_flag = nullptr, int *next_flag = nullptr,
-                 bool mask_first = false, bool packed = false, int pass_index = 0)
+                 bool mask_first = false, bool packed = false, int pass_index = 0, uint64_t turn = 0)
 {
     packed = packed && uses_gram(g.tc) && g.tc.pack != 0;
     const int b0 = pass_index % 3, b1 = (pass_index + 1) % 3, b2 = (pass_index + 2) % 3;
@@ -817,6 +825,7 @@ int enqueue_pass(pilot_ctx *ctx, const Plan &plan, const DevPtrs &dp, const Ws &
     a.hlev = ws.hlev;
     a.partials = ws.partials + g.partial_off;
     a.run_flag = run_flag;
+    a.count_slot = count_slot_of(g.level, turn);
     if (packed) {
         a.ppose = ws.ppose + (size_t)b0 * ws.hyps;
         a.pcount = ws.pcount + (size_t)b0 * ws.frames;
@@ -836,6 +845,7 @@ int enqueue_pass(pilot_ctx *ctx, const Plan &plan, const DevPtrs &dp, const Ws &
     e.hs = ws.hs;
     e.pairs = ws.pairs + g.stat_class;
     e.next_flag = next_flag;
+    e.step_spins = (ctx->flags & PILOT_FLAG_NO_STEP_WAIT) ? 0 : kStepSpins;
     e.mask_first = mask_first ? 1 : 0;
     if (packed) {
         e.phs = ws.phs + (size_t)b0 * ws.hyps;
@@ -932,7 +942,7 @@ int enqueue_schedule(pilot_ctx *ctx, const Plan &plan, const DevPtrs &dp, const 
                 // pass k of level l runs only if pass k - 1 left a hypothesis at level l
                 int *flags = ws.passflag + (size_t)l * plan.flag_stride;
                 int rc = enqueue_pass(ctx, plan, dp, wp, *g, MODE_LM, q ? ctx->side[q - 1] : s, timed, flags + k,
-                                      flags + k + 1, false, pack, k);
+                                      flags + k + 1, false, pack, k, k);
                 if (rc) return rc;
             }
             for (int i = 0; i < nside; ++i) {
@@ -1817,10 +1827,12 @@ int pilot_step(pilot_ctx *ctx)
     dp.tiles = (TileItem *)((char *)ctx->s_desc.p + ib);
     // a serving step runs every level over every active slot, so most tiles of
     // a launch are at other levels: its epilogues test the tile mask first
+    ctx->step_turn++;
     for (int l = 0; l < PILOT_MAX_LEVELS; ++l)
         for (const LaunchGroup &g : plan.groups)
             if (g.level == l && (rc = enqueue_pass(ctx, plan, dp, ws_of(ctx), g, MODE_LM, ctx->stream,
-                                                   (ctx->flags & PILOT_FLAG_PROFILE) != 0, nullptr, nullptr, true)))
+                                                   (ctx->flags & PILOT_FLAG_PROFILE) != 0, nullptr, nullptr, true, false, 0,
+                                                   ctx->step_turn)))
                 return rc;
     int prune_M = 0;
     for (const ServingSlot &sl : ctx->slots)
