@@ -42,5 +42,7 @@ def spilled(tmp_path):
 def test_pass_kernels_keep_their_loops_in_registers(tmp_path):
     s = spilled(tmp_path)
     assert len(s) > 100
-    many = {k: n for k, n in s.items() if n > 512 and k[0] not in (2, 9)}   # variant 2: as it always was
+    many = {k: n for k, n in s.items() if n > 512 and k[0] != 2}     # variant 2: as it always was
     assert not many, many
+    # 32 channels a lane and more of variants 9 and 10: the three-wave form
+    assert [s[9, 128, 1, 4], s[9, 64, 1, 2], s[9, 256, 1, 8]] == [0, 0, 0]
