@@ -450,7 +450,12 @@ __global__ __launch_bounds__(256) void finalize_kernel(const FrameDev *frames, c
 // from LDS: in one block that chain is M^2 / 256 iterations long (449 us for
 // the 1210-pose grid, over half of its solve), so a block takes kPruneChunk
 // hypotheses with kPruneLanes lanes each, every lane counting its share of
-// the frame (that solve went from 826 to 378 us).  The blocks of a frame
+// the frame (that solve went from 826 to 378 us), and up to kPruneMaxBlocks
+// blocks share a frame: with one per chunk, four served frames of 8192
+// hypotheses cost 50 to 107 us in every step that ranks nothing and 220 in the
+// one that does; with 128 blocks, and the words of a block's own hypotheses
+// read first, 5 to 12 and 153 (with 64 blocks 5 to 9 and 268, with 256 8 to 23
+// and 180; one block per frame 8 to 22 and 19400).  The blocks of a frame
 // do not wait for each other.  What one of them writes must not change what
 // the others read: they read costs, which no block writes, and the level
 // words, which go from HLEV_WAIT to the next level or to HLEV_PRUNED, both of
@@ -461,6 +466,7 @@ constexpr int kPruneMaxM = 8192;
 constexpr int kPruneBlock = 256;
 constexpr int kPruneLanes = 16;                       // lanes per ranked hypothesis
 constexpr int kPruneChunk = kPruneBlock / kPruneLanes;
+constexpr int kPruneMaxBlocks = 128;                  // per frame
 
 __global__ __launch_bounds__(kPruneBlock) void prune_kernel(const FrameDev *frames, HypState *hs, PoseEval *pose,
                                                             int *hlev)
@@ -469,44 +475,59 @@ __global__ __launch_bounds__(kPruneBlock) void prune_kernel(const FrameDev *fram
     const int m0 = blockIdx.x * kPruneChunk;
     if (f.M <= 0 || f.keep_top <= 0 || m0 >= f.M) return;
     __shared__ double s_cost[kPruneMaxM];
+    // most launches of a serving loop find nothing to rank: a block learns that
+    // from its own hypotheses' words, and that the frame is not ready from the
+    // frame's
+    const int stride = gridDim.x * kPruneChunk;
     int waiting = 0, busy = 0;
+    for (int k = threadIdx.x; k / kPruneChunk * stride < f.M - m0; k += kPruneBlock) {
+        const int own = m0 + k / kPruneChunk * stride + k % kPruneChunk;
+        waiting |= (own < f.M && hlev[f.hyp_base + own] == HLEV_WAIT);
+    }
+    if (!__syncthreads_or(waiting)) return;
     for (int m = threadIdx.x; m < f.M; m += kPruneBlock) {
         const int h = hlev[f.hyp_base + m];
-        waiting |= (h == HLEV_WAIT && m >= m0 && m < m0 + kPruneChunk);
         busy |= (h >= 0 && h <= f.prune_level);
+    }
+    if (__syncthreads_or(busy)) return;
+    for (int m = threadIdx.x; m < f.M; m += kPruneBlock) {
+        const int h = hlev[f.hyp_base + m];
         const bool ranked = h == HLEV_WAIT || h == f.prune_level + 1 || h == HLEV_PRUNED;
         const double c = hs[f.hyp_base + m].cost;
         s_cost[m] = ranked ? (isnan(c) ? __longlong_as_double(0x7ff0000000000000LL) : c)
                            : __longlong_as_double(0x7ff8000000000000LL);   // NaN: not ranked
     }
-    if (!__syncthreads_or(waiting) || __syncthreads_or(busy)) return;
-    const int m = m0 + (int)threadIdx.x / kPruneLanes, q = threadIdx.x % kPruneLanes;
-    const double cm = m < f.M ? s_cost[m] : __longlong_as_double(0x7ff8000000000000LL);
-    int better = 0;
-    if (!isnan(cm))
+    __syncthreads();
+    const int q = threadIdx.x % kPruneLanes;
+    for (int m = m0 + (int)threadIdx.x / kPruneLanes; m < f.M; m += stride) {   // lane groups leave together
+        const double cm = s_cost[m];
+        if (isnan(cm)) continue;
+        int better = 0;
         for (int j = q; j < f.M; j += kPruneLanes) {
             const double cj = s_cost[j];
             better += (cj < cm || (cj == cm && j < m)) ? 1 : 0;   // false for the unranked (NaN)
         }
 #pragma unroll
-    for (int o = kPruneLanes / 2; o >= 1; o >>= 1) better += __shfl_xor(better, o, 64);
-    if (q != 0 || isnan(cm) || hlev[f.hyp_base + m] != HLEV_WAIT) return;
-    HypState &s = hs[f.hyp_base + m];
-    if (better < f.keep_top) {
-        s.level = f.prune_level + 1;
-        s.phase = PHASE_START;
-        for (int i = 0; i < 12; ++i) pose[f.hyp_base + m].v[i] = s.T[i];
-        hlev[f.hyp_base + m] = s.level;
-    } else {
-        s.status = ST_PRUNED;
-        hlev[f.hyp_base + m] = HLEV_PRUNED;
+        for (int o = kPruneLanes / 2; o >= 1; o >>= 1) better += __shfl_xor(better, o, 64);
+        if (q != 0 || hlev[f.hyp_base + m] != HLEV_WAIT) continue;
+        HypState &s = hs[f.hyp_base + m];
+        if (better < f.keep_top) {
+            s.level = f.prune_level + 1;
+            s.phase = PHASE_START;
+            for (int i = 0; i < 12; ++i) pose[f.hyp_base + m].v[i] = s.T[i];
+            hlev[f.hyp_base + m] = s.level;
+        } else {
+            s.status = ST_PRUNED;
+            hlev[f.hyp_base + m] = HLEV_PRUNED;
+        }
     }
 }
 
 hipError_t launch_prune(const FrameDev *frames, int n_frames, int max_M, HypState *hs, PoseEval *pose, int *hlev,
                         hipStream_t s)
 {
-    const dim3 grid((std::min(max_M, kPruneMaxM) + kPruneChunk - 1) / kPruneChunk, n_frames);
+    const int chunks = (std::min(max_M, kPruneMaxM) + kPruneChunk - 1) / kPruneChunk;
+    const dim3 grid(std::min(chunks, kPruneMaxBlocks), n_frames);
     hipLaunchKernelGGL(prune_kernel, grid, dim3(kPruneBlock), 0, s, frames, hs, pose, hlev);
     return hipGetLastError();
 }
