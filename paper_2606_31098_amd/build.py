@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import concurrent.futures as cf
 import os
+import re
 import shutil
 import subprocess
 import sys
@@ -49,16 +50,27 @@ def source_digest() -> str:
     return h.hexdigest()[:16]
 
 
+def pass_kernel_sources():
+    """The files the pass kernels are compiled from: their translation units
+    and everything of csrc that those include."""
+    todo = [f for f in os.listdir(CSRC) if f.startswith("pilot_pass") and f.endswith(".hip")]
+    seen = set()
+    while todo:
+        f = todo.pop()
+        if f in seen or not os.path.exists(os.path.join(CSRC, f)):
+            continue
+        seen.add(f)
+        todo += re.findall(r'^\s*#\s*include\s+"([^"]+)"', open(os.path.join(CSRC, f)).read(), re.M)
+    return sorted(seen)
+
+
 def pass_kernel_digest() -> str:
-    """SHA-256 over the sources the pass kernels are compiled from (their
-    translation units and everything those include)."""
+    """SHA-256 over pass_kernel_sources() and the compiler's flags."""
     import hashlib
-    h = hashlib.sha256()
-    for f in sorted(os.listdir(CSRC)):
-        if (f.startswith("pilot_pass") and f.endswith((".hip", ".inc"))) or \
-                f in ("pilot_kernels.h", "pilot_lm.h", "pilot_device.h"):
-            h.update(f.encode())
-            h.update(open(os.path.join(CSRC, f), "rb").read())
+    h = hashlib.sha256(" ".join(HIP_FLAGS).encode())
+    for f in pass_kernel_sources():
+        h.update(f.encode())
+        h.update(open(os.path.join(CSRC, f), "rb").read())
     return h.hexdigest()[:16]
 
 
