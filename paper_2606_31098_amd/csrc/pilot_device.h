@@ -142,8 +142,8 @@ struct PassArgs {
     // the packed entries hb .. hb + G - 1 of the hypotheses still at the level
     // (pcount[frame] of them from the frame's hyp_base on; their poses under
     // evaluation are ppose[hb + hh]); tiles past that count have nothing to do.
-    // Block 0 clears pcount_clear[0 .. n_frames) (the counts the pass's
-    // epilogue appends to).
+    // Block 0 clears pcount_clear[0 .. n_frames): the counts that the next
+    // launch's steps append to, never EpilogueArgs::pcount_next.
     const PoseEval *ppose;
     const int *pcount;
     int *pcount_clear;

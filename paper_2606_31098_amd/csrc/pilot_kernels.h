@@ -12,7 +12,8 @@ struct TileConfig {
     int variant = 1;    // pass kernel: 1 batch-then-compute loop, 2 software-pipelined loop,
                         // 3-8 per-cell Gram tables (see pilot_pass3.inc), 9-10 the same with
                         // FP32 arithmetic on the per-pair path for bf16 maps (pilot_pass4.inc,
-                        // one kernel under both numbers)
+                        // one kernel under both numbers); which kernel f32 maps run under
+                        // a number: f32_variant (pilot_pass.inc)
     int pack = 0;       // variants 3-10: hypothesis tiles 0 contiguous, 1 packed when that saves
                         // rounds of blocks (use_packed), 2 packed whenever hypotheses remain
 };

@@ -23,6 +23,8 @@ bool pass_supported(int C, int dtype, int G)
 hipError_t launch_pass(int C, int dtype, const TileConfig &tc, const PassArgs &a, const EpilogueArgs &e,
                        hipStream_t s)
 {
+    // block 0 clears counts while the launch's steps append to others
+    if (a.pcount_clear && (a.pcount_clear == e.pcount_next || a.pcount_clear == a.pcount)) return hipErrorInvalidValue;
     switch (C) {
     case 16: return launch_pass_c16(dtype, tc, a, e, s);
     case 32: return launch_pass_c32(dtype, tc, a, e, s);

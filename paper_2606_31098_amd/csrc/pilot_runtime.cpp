@@ -3,7 +3,7 @@
 // A solve is planned on the host (validation, tile choice, work lists),
 // its descriptors are copied to the device once, and the whole
 // coarse-to-fine LM schedule -- init, then per level (1 + iters) x
-// [pass kernel -> epilogue kernel], then finalize -- is enqueued on the
+// [pass with its LM steps], then finalize -- is enqueued on the
 // context stream, replayed from a cached hipGraph when a solve with the same
 // plan shape was seen before.  No device->host traffic inside a solve.
 #include <hip/hip_runtime.h>
@@ -710,7 +710,7 @@ struct Ws {
     unsigned long long *pairs = nullptr;
     int *passflag = nullptr;
     // packed hypothesis tiles, three rotating buffers (pass k of a level reads
-    // buffer k % 3, its epilogue appends to (k + 1) % 3, and the pass clears the
+    // buffer k % 3, its LM steps append to (k + 1) % 3, and the pass clears the
     // counts of (k + 2) % 3): per frame the LM states of the hypotheses still at
     // the level, their poses under evaluation and their number
     HypState *phs = nullptr;     // 3 x hyps
@@ -803,7 +803,7 @@ int ensure_state(pilot_ctx *ctx, Plan &plan)
 // placed.
 constexpr int kStepSpins = 1 << 12;
 
-// Enqueue one pass (pass kernel + epilogue) of a launch group.
+// Enqueue one pass (item sums and LM steps) of a launch group.
 // packed: the Gram-table variants (3 to 10) walk packed hypothesis tiles,
 // built by the pack kernel right before the pass.
 int enqueue_pass(pilot_ctx *ctx, const Plan &plan, const DevPtrs &dp, const Ws &ws, const LaunchGroup &g, int mode,
@@ -896,7 +896,7 @@ int enqueue_schedule(pilot_ctx *ctx, const Plan &plan, const DevPtrs &dp, const 
                             nullptr, 0, s, ws.passflag, PILOT_MAX_LEVELS * plan.flag_stride, plan.flag_stride));
     // packed hypothesis tiles: the Gram-variant passes walk, G at a time, the
     // list of each frame's hypotheses still at the level (listed in index order
-    // at the level's start, then by each epilogue, which appends the ones that
+    // at the level's start, then by each pass's LM steps, which append the ones that
     // stay), so a pass costs what its live hypotheses need rather than every
     // tile that still holds one.  Sums do not depend on a hypothesis' tile or
     // slot, so results are those of contiguous tiles, bit for bit.
@@ -906,7 +906,7 @@ int enqueue_schedule(pilot_ctx *ctx, const Plan &plan, const DevPtrs &dp, const 
     Ws wp = ws;
     wp.hyps = std::max(1, plan.total_hyps);
     wp.frames = std::max(1, nf);
-    // a level's first pass reads buffer 0, filled here; its epilogue appends
+    // a level's first pass reads buffer 0, filled here; its LM steps append
     // to buffer 1, and the next pass clears buffer 2
     auto pack_level = [&](int level) -> hipError_t {
         return launch_pack(dp.frames, nf, plan.max_M, wp.hlev, level, wp.hs, wp.pose, wp.phs, wp.ppose, wp.pcount,
@@ -1826,7 +1826,7 @@ int pilot_step(pilot_ctx *ctx)
     dp.items = (WorkItem *)ctx->s_desc.p;
     dp.tiles = (TileItem *)((char *)ctx->s_desc.p + ib);
     // a serving step runs every level over every active slot, so most tiles of
-    // a launch are at other levels: its epilogues test the tile mask first
+    // a launch are at other levels: epilogue launches test the tile mask first
     ctx->step_turn++;
     for (int l = 0; l < PILOT_MAX_LEVELS; ++l)
         for (const LaunchGroup &g : plan.groups)
