@@ -165,8 +165,8 @@ struct EpilogueArgs {
     HypState *hs;
     unsigned long long *pairs;   // evaluated anchor x hypothesis pairs of this launch's class
     int *next_flag;              // NULL, or set to 1 when a hypothesis stays at this level
-    int step_spins;              // turns (at least 0.3 us each) that a step block waits for its
-                                 // tile's items before it walks them itself
+    unsigned long long step_wait;   // wall clock ticks that a step block waits for its tile's items
+                                 // before it walks them itself; 0: does not wait
     int mask_first;              // test the tile mask before fetching the partial sums (launches
                                  // where most tiles are at other levels), else after
     // packed hypothesis tiles (as in PassArgs), or NULL: slot hh of the tile

@@ -57,6 +57,7 @@ struct LaunchGroup {
     int passes = 0;
     int stat_class = 0;
     size_t partial_off = 0;   // its partial records in the partials buffer (floats)
+    uint64_t pairs = 0;       // anchors x hypotheses of its frames
 };
 
 // Side streams of a context: the launch groups of one pass run concurrently
@@ -643,6 +644,7 @@ void build_plan(const pilot_ctx *ctx, const pilot_frame *frames, int n, const pi
                 const TileConfig &t = tci[i];
                 const int nht = (frames[i].M + t.G - 1) / t.G;
                 const int npt = n_ptiles_of(t, frames[i].level[l].N);
+                g.pairs += (uint64_t)frames[i].level[l].N * frames[i].M;
                 if (nht * npt > most_items) most = i, most_items = nht * npt;
                 for (int ht = 0; ht < nht; ++ht) {
                     const int h0 = ht * t.G, nh = std::min(t.G, frames[i].M - h0);
@@ -796,12 +798,17 @@ int ensure_state(pilot_ctx *ctx, Plan &plan)
     return PILOT_OK;
 }
 
-// Turns (about 0.4 us each) that a step block waits for its tile's items before
-// it walks them itself.  It starts when the last items of its XCD have started,
-// so it waits for about one item (5 to 100 us, tens of items where other
-// launches share the device); past 1.6 ms its items are most likely not even
-// placed.
-constexpr int kStepSpins = 1 << 12;
+// How long a step block waits for its tile's items before it walks them itself,
+// in ticks of the 100 MHz wall clock: 2 ms and 2 ns per pair of the launch, ten
+// times what the slowest kernels take alone.  An XCD whose items are the
+// cheaper ones is done with them early, by a fifth of the launch's time where
+// one XCD has the ragged anchor tiles, and its step blocks wait that long for
+// the others (2048 hypotheses x 40000 anchors, 3.1 ms a pass: 0.6 ms; with that
+// time as the limit the pass took 5.2).
+uint64_t step_wait_of(const pilot_ctx *ctx, uint64_t pairs)
+{
+    return (ctx->flags & PILOT_FLAG_NO_STEP_WAIT) ? 0 : 200000 + pairs / 5;
+}
 
 // Enqueue one pass (item sums and LM steps) of a launch group.
 // packed: the Gram-table variants (3 to 10) walk packed hypothesis tiles,
@@ -845,7 +852,7 @@ int enqueue_pass(pilot_ctx *ctx, const Plan &plan, const DevPtrs &dp, const Ws &
     e.hs = ws.hs;
     e.pairs = ws.pairs + g.stat_class;
     e.next_flag = next_flag;
-    e.step_spins = (ctx->flags & PILOT_FLAG_NO_STEP_WAIT) ? 0 : kStepSpins;
+    e.step_wait = step_wait_of(ctx, g.pairs);
     e.mask_first = mask_first ? 1 : 0;
     if (packed) {
         e.phs = ws.phs + (size_t)b0 * ws.hyps;
@@ -1651,6 +1658,7 @@ int serving_rebuild(pilot_ctx *ctx)
                 const TileConfig &t = tck[k];
                 const int nht = (frames[k].M + t.G - 1) / t.G;
                 const int npt = n_ptiles_of(t, frames[k].level[l].N);
+                g.pairs += (uint64_t)frames[k].level[l].N * frames[k].M;
                 if (nht * npt > most_items) most = k, most_items = nht * npt;
                 for (int ht = 0; ht < nht; ++ht) {
                     const int h0 = ht * t.G, nh = std::min(t.G, frames[k].M - h0);

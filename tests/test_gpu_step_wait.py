@@ -105,6 +105,32 @@ def test_steps_that_do_not_wait_serve_and_batch_the_same(tmp_path):
         ctx.close()
 
 
+def test_long_launches_wait_for_their_items():
+    """A pass of many milliseconds, whose XCDs end one or two apart: the step
+    blocks of the early ones have to wait, rather than walk their tiles alone one
+    item after the other (this pass then took 30 ms instead of 18)."""
+    from paper_2606_31098_amd.pilot import Context, DeviceFrame
+    M, ms = 2048, {}
+    ctx = Context(0)
+    for N in (4000, 40000):                         # neither is sorted
+        f = S.make_frame(2, 0, N=N, M=M, level_shapes=((480, 640, 128),), iters=(1,), dsm_side=448, seed=3)
+        d = DeviceFrame(f)
+        assert "G=8 PPG=16" in ctx.tile_choice(128, 0, N, M, 480 * 640)
+        poses = torch.as_tensor(f.poses, device="cuda")
+        best = 1e9
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            ctx.linearize(d, 0, poses)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        ms[N] = best
+    ctx.close()
+    say(f"long launches: {ms}")
+    assert ms[40000] < 1.35 * 10 * ms[4000], ms
+
+
 def test_large_solves_on_two_streams_at_once():
     """Two contexts, each on its own thread and stream, with 1024 hypothesis
     tiles a pass: more step blocks than an XCD holds blocks of both."""
